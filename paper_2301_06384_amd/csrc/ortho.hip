@@ -455,6 +455,12 @@ gram_f32mma_kernel(int64_t n, int ld, const float* __restrict__ Abase, int64_t a
     __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)a,
                                      (__attribute__((address_space(3))) void*)lds, 16, 0, 0);
   };
+  // the barrier before a buffer is read: loads to LDS are counted with the
+  // wavefront's memory loads, which a barrier alone does not wait for
+  auto landed = [&]() {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+  };
   // rows r0 .. of full rounds; of the last one when fewer are left, its rows
   // past the range read the last row
   auto load = [&](int64_t r0, int p) {
@@ -483,7 +489,7 @@ gram_f32mma_kernel(int64_t n, int ld, const float* __restrict__ Abase, int64_t a
 #pragma unroll
       for (int q = 0; q < 4; ++q) a64[ti][tj][q] = 0.0;
   if (rb < re) load(rb, 0);
-  __syncthreads();
+  landed();
   int p = 0;
   for (int64_t r0 = rb; r0 < re; r0 += MG_RS) {
     if (r0 + MG_RS < re) {
@@ -518,7 +524,7 @@ gram_f32mma_kernel(int64_t n, int ld, const float* __restrict__ Abase, int64_t a
       for (int tj = 0; tj < 2; ++tj)
 #pragma unroll
         for (int q = 0; q < 4; ++q) a64[ti][tj][q] += (double)acc[ti][tj][q];
-    __syncthreads();
+    landed();
     p ^= 1;
   }
   double* P = part + (int64_t)tc * pa * ld;

@@ -1188,7 +1188,9 @@ uint64_t footprint_bytes(int64_t n, int s, int m, int variant, int precision, ui
     return (uint64_t)b;
   }
   if (variant == GK_CHEB || variant == GK_CHEB2) {
-    b = blk8 * (variant == GK_CHEB2 ? 5 : 4);
+    // the two blocks of the recurrence, with cheb^2 the result of its first
+    // application, and the column of each row in E_W
+    b = blk8 * (variant == GK_CHEB2 ? 3 : 2) + 4.0 * n;
   } else {
     b = mixed ? (3 * blk8 + m * blk8 / 2) : m * blk8;
     b += 2 * blk8;   // X, Y
@@ -1198,7 +1200,7 @@ uint64_t footprint_bytes(int64_t n, int s, int m, int variant, int precision, ui
       // eigendecompositions of the tridiagonal matrices, and the estimates
       const double nw = variant == GK_GBL ? 1.0 : (double)s;
       b += 8.0 * coldots_scratch_elems(n, m, ld) + 2.0 * m * ld * 8.0 + 2.0 * m * nw * 8.0 + 3.0 * nw * 8.0;
-      b += nw * (2.0 * m * m + 2.0 * m) * 8.0 + 8.0 * 2.0 * eig_order_elems(m, (int)nw);
+      b += nw * (2.0 * m * m + 2.0 * m) * 8.0 + 8.0 * eig_order_elems(m, (int)nw);
       b += 3.0 * m * nw * 8.0 + 8.0 * m * ld;
     }
     if (variant == GK_CBL) {

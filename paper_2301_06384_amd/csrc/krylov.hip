@@ -9,7 +9,8 @@
 //
 // Precision paths
 //   GK_FP64  : all blocks float64; each new block is orthogonalised against
-//              its two predecessors and then twice against the whole basis.
+//              its two predecessors and then against the whole basis, twice
+//              where the first projection was not small (launch_again).
 //   GK_MIXED : the three-term recurrence (current and previous block, X) and
 //              all small factors stay float64, the operator uses float32
 //              weights and the basis is archived in float32 for the
@@ -527,14 +528,6 @@ struct CblRun {
   // projection and its Gram run only then
   int* again = nullptr;
   bool gated() const { return again != nullptr; }
-  // Steps at the end of a call that project once.  A rounding of the basis grows
-  // on its way to the columns: with the gate on all 40 steps (100k nodes, s = 64,
-  // spline), 3 of 76 sample sets ended more than 1e-9 from the columns of the
-  // path that always projects twice, the worst 7e-9; from 20 steps before the end
-  // those end within 7e-13.  The steps before have the short bases: 40.0 ms with
-  // the gate everywhere, 49.0 so, 70.2 without.  Narrower blocks gate every step
-  // (their products round differently anyway; at most 2e-10 over 40 sets, m = 40).
-  static constexpr int kOnceSteps = 20;
   // GK_FP64 at widths 8 to 48: the products with the stored basis, and at 8
   // every product, run in narrow.hip
   bool nar = false, nar8 = false;
@@ -672,7 +665,7 @@ struct CblRun {
     const double* V1 = k > 0 ? Vk : nullptr;
     // (no second local pass ahead of the projection against the whole basis,
     // which covers these blocks)
-    const bool once = gated() && k >= 1 && (nar || m - k <= kOnceSteps);
+    const bool once = gated() && k >= 1;
     const int local_passes = mixed || once ? 1 : 2;
     // GK_MIXED (block widths up to 512) takes the recurrence as written in
     // Alg. 1: X = L Q_k - Q_{k-1} H_{k-1,k} with H_{k-1,k} = B_{k-1}^T from the

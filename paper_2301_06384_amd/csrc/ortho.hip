@@ -809,12 +809,22 @@ void launch_gram(int64_t n, int ld, BlockList A, const double* B, double* C, dou
 // Does the projection X1 = X - Q C have to be repeated?  Not when it took
 // away at most 1e-8 of every column of X1 (G: the Gram matrix of X1): what it
 // leaves along the basis is (I - Q^T Q) C, below the rounding of X1 itself,
-// which a second projection has as well.  Repeating only then (in a call's last
-// steps, CblRun::kOnceSteps), and leaving out the second local pass ahead of it,
-// took a float64 call (100k-node geometric graph, s = 64, m = 40) from 70.2 to
-// 49.0 ms.  Workgroup (j, y): block j, columns
-// 16 y ..; a column not known to be small (NaN too) sets the flag, which the
-// caller has cleared.
+// which a second projection has as well.  So a step that passes this test is as
+// orthogonal as one that projects twice, whatever its place in the call and the
+// width of its block, and every float64 step takes it, with one local pass ahead.
+// The columns then differ from those of two projections by roundings.  Where
+// the method amplifies roundings (columns not converged yet), by as much as two
+// projections change when the nodes are renumbered: geometric graphs, spline, of
+// the columns' norm, largest over the sample sets, renumbered | once:
+//   100k, s = 64: m = 40 (100 sets) 1.6e-10 | 2.1e-10, m = 80 7.3e-5 | 7.3e-5
+//   100k, m = 60..200: s = 48 1.7e-7 | 1.6e-7, 16 1.3e-4 | 1e-4, 1 6.6e-7 | 5.4e-7
+//   50k, s = 20: sbl m = 80 6.2e-8 | 7.7e-8, gbl m = 150 6.6e-6 | 3.2e-6
+// with the same distance to phi(L) in all digits shown (2.8e-5 to 0.75).  Against
+// the method in extended precision, twice, renumbered | once: 20k, s = 64, m = 80
+// 1.4e-8, 1.9e-8 | 1.6e-8; s = 16, m = 100 2.8e-5, 3.1e-5 | 2.9e-5.
+// 100k, s = 64, m = 40: 70.6 ms a call twice, 40.1 so.  Workgroup (j, y): block j,
+// columns 16 y ..; a column not known to be small (NaN too) sets the flag, which
+// the caller has cleared.
 __global__ void __launch_bounds__(256)
 again_kernel(int nb, int ld, int s, const double* __restrict__ C, const double* __restrict__ G, int* __restrict__ flag) {
   __shared__ double red[256];

@@ -77,3 +77,21 @@ def test_sampled_block(variant, s):
                 assert np.linalg.norm(K - ref) < tol * np.linalg.norm(ref), (m, prec)
     finally:
         g.release()
+
+
+# elsewhere a step projects once, early and late in the call: the work of the
+# launches that were not skipped is that of one projection a step
+@pytest.mark.parametrize("m", [12, 30, 45])
+def test_one_projection_a_step(m):
+    n, s = 12_000, 64
+    L = I.rgg_knn(n, 8, seed=7)
+    g = gk.Graph.from_laplacian(L, flags=gk.REORDER)
+    try:
+        W, phi = I.samples(n, s, 2), dict(kind="diffusion", t=0.6)
+        gk.krylov_kernel_columns(g, W, phi, m, "cbl", "fp64", flags=gk.TIMING)
+        work = {r["name"]: r["alg_flops"] for r in gk.kernel_timings()}
+        # the first Gram pass of step k reads k + 1 blocks, and its X^T X one triangle
+        assert work["tsgemm"] == sum(2.0 * n * s * s * (k + 1) for k in range(1, m))
+        assert work["gram"] == sum(2.0 * n * s * s * (k + 1) + n * s * (s + 1.0) for k in range(1, m))
+    finally:
+        g.release()

@@ -205,7 +205,7 @@ void launch_reduce_parts(int64_t len, int nparts, const double* part, double* ou
 // Blocks 64 and wider use the FP64 matrix-core kernels below (rows staged
 // 32 at a time, 64-wide output tiles); narrower ones the vector kernel above.
 static bool mfma_ok(int ld) { return ld >= 64 && ld % 16 == 0; }
-constexpr int MG_T = 64, MG_RS = 32, MG_P = MG_T + 2;
+constexpr int MG_T = 64, MG_RS = 32;
 
 static void gram_geometry(int64_t n, int nb, int ld, int* nx, int* ny, int* nch, int64_t* rpc) {
   const int rs = mfma_ok(ld) ? MG_RS : G_RS;

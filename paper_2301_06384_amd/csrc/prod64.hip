@@ -254,21 +254,27 @@ void launch_gram64(int64_t n, int ld, BlockList A, const double* B, double* part
 #define GK_G(UA_, UB_, K_, PAIRS_)                                                                                  \
   hipLaunchKernelGGL((gram64_kernel<UA_, UB_, K_>), dim3((unsigned)nch * (unsigned)(PAIRS_)), dim3(64 * UA_), 0, st, \
                      n, ld, u, (const double*)A.base, A.stride, nua, B, part, rpc, nta, nt, flag)
-#define GK_T(T_)                                                  \
-  case T_:                                                        \
-    if (few) GK_G(4, 4, GK_ALL, nta * nt);                        \
-    else if (!self) GK_G(8, T_, GK_ALL, nta * nt);                \
-    else GK_G(T_, T_, GK_SELF, nt);                               \
-    if (self && nt > 1) GK_G(T_, T_, GK_OFF, nt * (nt - 1) / 2);   \
+#define GK_T(T_)                                   \
+  case T_:                                         \
+    if (few) GK_G(4, 4, GK_ALL, nta * nt);         \
+    else if (!self) GK_G(8, T_, GK_ALL, nta * nt); \
+    else GK_G(T_, T_, GK_SELF, nt)
+  // a block with itself in several tiles (of 4 to 6 units): the pairs off the diagonal
+#define GK_TO(T_)                                                    \
+    GK_T(T_);                                                        \
+    if (self && nt > 1) GK_G(T_, T_, GK_OFF, nt * (nt - 1) / 2);     \
     break
   switch (T) {
-    GK_T(4);
-    GK_T(5);
-    GK_T(6);
+    GK_TO(4);
+    GK_TO(5);
+    GK_TO(6);
     GK_T(7);
+    break;
     GK_T(8);
+    break;
     default: throw Error{GK_EUNSUPPORTED, "float64 Gram: unsupported block width"};
   }
+#undef GK_TO
 #undef GK_T
 #undef GK_G
   GK_HIP(hipGetLastError());

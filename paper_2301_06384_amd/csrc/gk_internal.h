@@ -194,14 +194,17 @@ size_t coldots_scratch_elems(int64_t n, int nb, int ld);
 // out[k*ld + c] = sum_i A_k[i,c] * B[i,c]
 void launch_coldots(int64_t n, int ld, BlockList A, const double* B, double* out, double* part,
                     const int* flag, hipStream_t st);
-// X[i,c] -= sum_k D[k*ld + c] * A_k[i,c]
+// X -= A diag(D) for one or two float64 blocks A, and of the new X in the same
+// pass: out = A_0^T X, .. (dots; column dot products), X^T X
 void launch_axpy_dots(int64_t n, int ld, BlockList A, const double* D, double* X, bool dots, double* out, double* part,
                       hipStream_t st);
+// X -= A diag(D) for float64 blocks A, and the squared column norms of X
 void launch_axpy_norms(int64_t n, int ld, BlockList A, const double* D, double* X, double* nrm, double* part,
                        const int* flag, hipStream_t st);
 // as launch_again, for column coefficients D and squared column norms nrm
 void launch_again_diag(int nb, int ld, int s, bool global, const double* D, const double* nrm, int* flag,
                        hipStream_t st);
+// X[i,c] -= sum_k D[k*ld + c] * A_k[i,c]
 void launch_axpy_diag(int64_t n, int ld, BlockList A, const double* D, double* X, const int* flag,
                       hipStream_t st);
 // Y[i,c] = X[i,c] * scale[c] (and optional float copy)

@@ -1,8 +1,11 @@
 // FP64 tile products on v_mfma_f64_4x4x4_4b, the FP64 matrix instruction that
-// reaches the part's FP64 rate: register-only loops measured 73 TFLOP/s with
-// it (69 at four independent accumulators), from one wavefront per SIMD on,
-// against 47 (two or more wavefronts per SIMD; 35 at one) with
-// v_mfma_f64_16x16x4.
+// reaches the part's FP64 rate.  Register-only loops on one card, TFLOP/s at 1
+// and at 2..8 wavefronts per SIMD, by independent accumulators:
+//                      1            2            4            8
+//   4x4x4_4b       61, 77       76, 77       77, 77       77, 77
+//   16x16x4        68, 73-74    67, 71-72    60, 66-68    49, 59-60
+// An accumulator of the wide form is four registers a lane, so a tile of several
+// units has the larger counts.
 //
 // One instruction forms four independent 4 x 4 products (blocks b) over four
 // contraction indices; lane l = j + 4 b + 16 k holds A_b[j][k] and B_b[k][j],

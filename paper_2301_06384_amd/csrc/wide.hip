@@ -98,6 +98,12 @@ __device__ __forceinline__ void wterm(double (&tot)[4][4], double sign, const do
 // the chain is a 64 x 64 Cholesky and three tile products a step.
 // Bound by that chain.  In one workgroup the n^3 work ran at the rate of one of
 // 256 compute units: s = 512: 2.4 ms, now 0.33; s = 128: 165 us, now 110.
+// The launches are the faster form down to the narrowest widths here, also where
+// the second pass is switched off (empty launches).  One workgroup | launches, ms
+// of CholQR in a call of 19 steps, 20k nodes: s = 65 float64 3.40 | 2.42, mixed
+// (17 second passes off) 2.24 | 1.78; s = 80 3.41 | 2.45, 2.45 | 1.78; s = 96 3.89 |
+// 2.76, 2.71 | 1.85.  Factor and k = 2 substitutions of the spline, 20 blocks:
+// s = 65 3.57 | 2.45, s = 96 4.07 | 2.71.
 //
 // Launch k reads the tiles of column k (L_kk, Y_kk and A_ik).  Storage: A and
 // Y hold their diagonal tiles (L_kk, Y_kk) and, below them, the tiles still

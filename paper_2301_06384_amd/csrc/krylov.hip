@@ -1122,9 +1122,13 @@ static void run_cheb(Job& J, bool squared) {
   // Clenshaw's recurrence b_k = a_k E + 2 x b_{k+1} - b_{k+2} with x = I -
   // (2/Lam) L, and p(x) E = a_0 E + x b_1 - b_2: three blocks of traffic a
   // step where the forward recurrence with its running sum moves five (301 x
-  // 301 grid, 50 columns, degree 60: 2.05 ms).  E = E_W is the start block,
-  // given by its columns (the second application of cheb^2: the dense result
-  // of the first).  b_k overwrites b_{k+2}.
+  // 301 grid, 50 columns, degree 60: 2.05 -> 1.45 ms).  Its roundings against
+  // extended precision, float64 columns on four kinds of graphs: 1.07 times the
+  // forward recurrence's in the median over degrees 10 to 1500, up to degree 80
+  // at most 2.1e-14 (1.9e-14); on a unit grid with Lam = 8, where the forward
+  // products are all but exact, up to 11 times (7.4e-15 against 6.7e-16).
+  // E = E_W is the start block, given by its columns (the second application of
+  // cheb^2: the dense result of the first).  b_k overwrites b_{k+2}.
   double* bA = J.ar.get<double>(blk);
   double* bB = J.ar.get<double>(blk);
   double* Pa = J.ar.get<double>(squared ? blk : 1);

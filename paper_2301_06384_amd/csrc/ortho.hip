@@ -820,8 +820,9 @@ void launch_gram(int64_t n, int ld, BlockList A, const double* B, double* C, dou
 //   100k, m = 60..200: s = 48 1.7e-7 | 1.6e-7, 16 1.3e-4 | 1e-4, 1 6.6e-7 | 5.4e-7
 //   50k, s = 20: sbl m = 80 6.2e-8 | 7.7e-8, gbl m = 150 6.6e-6 | 3.2e-6
 // with the same distance to phi(L) in all digits shown (2.8e-5 to 0.75).  Against
-// the method in extended precision, twice, renumbered | once: 20k, s = 64, m = 80
-// 1.4e-8, 1.9e-8 | 1.6e-8; s = 16, m = 100 2.8e-5, 3.1e-5 | 2.9e-5.
+// the method in extended precision, twice, renumbered | once: the set of the first
+// line that moved most 8.1e-10, 7.2e-10 | 1.4e-10; 20k, s = 64, m = 80 1.4e-8,
+// 1.9e-8 | 1.6e-8; 20k, s = 16, m = 100 2.8e-5, 3.1e-5 | 2.9e-5.
 // 100k, s = 64, m = 40: 70.6 ms a call twice, 40.1 so.  Workgroup (j, y): block j,
 // columns 16 y ..; a column not known to be small (NaN too) sets the flag, which
 // the caller has cleared.
